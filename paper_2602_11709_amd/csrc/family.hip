@@ -411,9 +411,10 @@ void launch_peak_families(const HChunk *chunks, int64_t n_chunks, const FamOps *
                           const int64_t *first, const int32_t *mult, const int64_t *perm, const int16_t *h,
                           const int16_t *k, const int16_t *l, int rule, int32_t *n_fam, int32_t *fam_of,
                           int64_t *fam_label, int32_t *fam_mult, hipStream_t s) {
-  if (n_chunks <= 0) return;
-  hipLaunchKernelGGL(k_peak_families, dim3((unsigned)n_chunks), dim3(kThreads), 0, s, chunks, fam_ops, peak_offset,
-                     first, mult, perm, h, k, l, rule, n_fam, fam_of, fam_label, fam_mult);
+  launch_ranges(n_chunks, kThreads, [&](int64_t begin, int64_t count) {
+    hipLaunchKernelGGL(k_peak_families, dim3((unsigned)count), dim3(kThreads), 0, s, chunks + begin, fam_ops,
+                       peak_offset, first, mult, perm, h, k, l, rule, n_fam, fam_of, fam_label, fam_mult);
+  });
 }
 
 }  // namespace xrd

@@ -219,6 +219,16 @@ __device__ __forceinline__ SegBlock seg_block(int64_t b, int segs) {
 }
 #endif
 
+// A launch holds fewer than 2^32 threads (beyond, its last blocks do not run and
+// no error tells).  Calls launch(first, count) over the items [0, n), of
+// ``threads`` threads each (below 2^32), in ranges below that: for launches that
+// grow with the batch's grids or capacity.
+template <class Launch>
+inline void launch_ranges(int64_t n, int64_t threads, Launch launch) {
+  const int64_t most = (((int64_t)1 << 32) - 1) / threads;
+  for (int64_t first = 0; first < n; first += most) launch(first, n - first < most ? n - first : most);
+}
+
 void launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 
 // Device address of the fixed scratch array (kNoallocBytes, 256-byte
