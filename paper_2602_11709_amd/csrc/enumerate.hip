@@ -332,9 +332,12 @@ __device__ void pack_crystal(int c, int lane, int32_t *cursor, const CrystalPlan
       AtomRec a{};
       AtomRot z{};
       if (active) {
-        a.x = in.x;
-        a.y = in.y;
-        a.z = in.z;
+        // a far coordinate without its whole cells (exactly): the plain path's
+        // circular functions reduce phases of up to 2^50 of their table's steps
+        auto near = [](double v) { return fabs(v) > 0x1p20 ? v - rint(v) : v; };
+        a.x = near(in.x);
+        a.y = near(in.y);
+        a.z = near(in.z);
         a.occ = in.occ;
         // an infinite B as a finite one of the same factors (the kernels' 2^x
         // takes finite exponents); not-a-number stays
