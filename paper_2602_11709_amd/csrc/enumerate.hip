@@ -339,9 +339,9 @@ __device__ void pack_crystal(int c, int lane, int32_t *cursor, const CrystalPlan
         a.y = near(in.y);
         a.z = near(in.z);
         a.occ = in.occ;
-        // an infinite B as a finite one of the same factors (the kernels' 2^x
-        // takes finite exponents); not-a-number stays
-        a.bfac = in.bfac > 1e300 ? 1e300 : in.bfac < -1e300 ? -1e300 : in.bfac;
+        // a huge B as one of the same factors, 0 or infinity (the kernels' 2^x
+        // takes exponents up to 1e60); not-a-number stays
+        a.bfac = in.bfac > 1e30 ? 1e30 : in.bfac < -1e30 ? -1e30 : in.bfac;
         a.log2occ = __log2f((float)a.occ);
         a.bl2e = (float)a.bfac * kLog2e;
         // the row recurrence's factors: e^{2 pi i z} and e^{-B G*33 / 2}
