@@ -440,7 +440,7 @@ void launch_broaden_caglioti(bool mixed, const CrystalPlan *plan, int64_t n_c, c
                              double *y, hipStream_t s);
 // The same over the span tables (n at most the batch's grid capacity), with the
 // lines formed once in ``lines`` (8 bytes per entry each; z holds (z, ql) in
-// single precision under MIXED).  Declared weak, as the launches above are not:
+// single precision under MIXED, ql in the plain path).  Declared weak, as the launches above are not:
 // host-only builds of the planner may leave it out.
 struct CagLines {
   double *w, *half, *wl, *z;
