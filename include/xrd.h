@@ -117,8 +117,9 @@ typedef struct {
                                      xrd_pattern_backward then fails with XRD_ERR_UNSUPPORTED */
     int32_t sf_rpt;               /* tile shape of the direct structure-factor sums: reflections
                                      per lane, 1, 2 or 4 (a wavefront sums a tile of 64 times
-                                     that); 0 selects 2 and lets xrd_autotune choose.  The
-                                     workspace is sized for any shape. */
+                                     that); 0 selects 2 and lets xrd_autotune choose (until it
+                                     has, a small batch's forward sums go by 1, to the same
+                                     bits).  The workspace is sized for any shape. */
 } xrd_batch_desc;
 
 typedef struct {

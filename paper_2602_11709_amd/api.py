@@ -135,8 +135,8 @@ class XrdBatch:
     "auto" (the recurrence for crystals with many atoms and long rows).
     ``forward_only`` leaves out the adjoint's tables and buffers (no
     ``pattern_backward`` on this batch).  ``sf_rpt`` fixes the tile shape of
-    the direct sums (reflections per lane: 1, 2 or 4); 0 starts at 2 and lets
-    ``autotune`` choose."""
+    the direct sums (reflections per lane: 1, 2 or 4); 0 starts at 2 (at 1 in a
+    small batch's forward sums) and lets ``autotune`` choose."""
 
     def __init__(self, batch: CrystalBatch, precision: str = "mixed", friedel: Optional[bool] = None,
                  rel_threshold: float = 0.0, device="cuda", frac: Optional[torch.Tensor] = None,

@@ -59,6 +59,7 @@ struct xrd_batch {
   int64_t sf_heavy = 0, sf_heavy_bw = 0;  // leading items that take a block each
   int32_t split_fwd = kSplitFwd, split_bw = kSplitBw;
   int32_t rpt = kSfRptDefault;      // reflections per lane of the direct structure-factor kernels
+  bool rpt_chosen = false;          // by the caller or xrd_autotune
   std::vector<double> expect_eval;  // per crystal: expected evaluated reflections
   int64_t grid_cap = 0;   // largest grid of a broadened-pattern call
   int64_t span_cap = 0;   // span-table entries per crystal: ceil(grid_cap / kSpanPts)
@@ -777,6 +778,7 @@ int xrd_batch_create(const xrd_batch_desc *d, xrd_batch **out) {
   // one item), so the heaviest work is dispatched first
   descending([&](int64_t c) { return b->atom_offset[c + 1] - b->atom_offset[c]; }, &b->sf_order);
   b->expect_eval = expect_eval;
+  b->rpt_chosen = d->sf_rpt != 0;
   set_tiles(b, d->sf_rpt == 0 ? kSfRptDefault : d->sf_rpt);
   const bool adjoint = d->forward_only == 0;
   for (int32_t c : b->sf_order) {
@@ -1138,7 +1140,7 @@ static void launch_forward_sums(xrd_batch *b, void *ws, const xrd_refl *r, void 
     launch_sf(mixed, friedel, at<SfItem>(ws, L.sf_items), (int64_t)b->sf_items.size(), b->sf_heavy,
               at<CrystalPlan>(ws, L.plan), r->refl_offset, r->h, r->k, r->l, r->q, r->lp, at<AtomRec>(ws, L.atoms),
               at<SpeciesRun>(ws, L.runs), at<int32_t>(ws, L.run_count), b->desc.sf_coeff, at<CoeffF>(ws, L.coeff_f),
-              A, B, I, deriv, b->rpt, sd);
+              A, B, I, deriv, b->rpt + (b->rpt_chosen ? kTileFixed : 0), sd);
   if (f.side) {
     (void)hipEventRecord(f.join, f.side);
     (void)hipStreamWaitEvent(s, f.join, 0);
@@ -1547,6 +1549,7 @@ int xrd_autotune(xrd_batch *b, void *ws, const xrd_refl *r, int32_t *split_out) 
     } best{b->rpt, b->split_fwd, b->split_bw, b->rec_min_atoms};
     float best_ms = 0.f;
     bool first = true;
+    b->rpt_chosen = true;
     for (int32_t rpt : shapes) {
       if (e != hipSuccess) break;
       set_tiles(b, rpt);

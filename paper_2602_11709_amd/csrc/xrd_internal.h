@@ -292,7 +292,10 @@ void launch_enumerate(const CrystalPlan *plan, int64_t n_c, const EnumChunk *chu
 // Items: the first n_heavy take a block each (atoms split over its four
 // wavefronts), the rest one wavefront each.  A non-null deriv_cache
 // ([refl_cap] float4 under mixed precision, else double4) receives
-// (A, B, dA/ds^2, dB/ds^2) of every evaluated reflection.
+// (A, B, dA/ds^2, dB/ds^2) of every evaluated reflection.  ``rpt``: reflections
+// per lane of the items' tiles, plus kTileFixed where the caller or xrd_autotune
+// chose them, which are then launched as they are.
+constexpr int kTileFixed = 8;
 void launch_sf(bool mixed, bool friedel, const SfItem *items, int64_t n_items, int64_t n_heavy, const CrystalPlan *plan,
                const int64_t *refl_offset, const int16_t *h, const int16_t *k, const int16_t *l, const double *q,
                const double *lp, const AtomRec *atoms, const SpeciesRun *runs, const int32_t *run_count,
