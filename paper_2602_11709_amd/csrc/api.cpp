@@ -1673,7 +1673,7 @@ int xrd_pattern_caglioti(xrd_batch *b, void *ws, const xrd_refl *r, const double
   const WsLayout &L = b->ws;
   const bool mixed = b->desc.precision == XRD_MIXED, friedel = b->desc.friedel != 0;
   const CrystalPlan *plan = at<CrystalPlan>(ws, L.plan);
-  if (g->n_points <= b->grid_cap && launch_caglioti_spans) {
+  if (g->n_points <= b->grid_cap) {
     // the merge's staging holds the lines (it is free between merges)
     const CagLines lines{at<double>(ws, L.ent_w), at<double>(ws, L.tmp_tt), at<double>(ws, L.tmp_i),
                          at<double>(ws, L.tmp_first)};

@@ -9,6 +9,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <stdlib.h>
 
 namespace xrd {
 
@@ -443,16 +444,22 @@ void launch_broaden_caglioti(bool mixed, const CrystalPlan *plan, int64_t n_c, c
                              double *y, hipStream_t s);
 // The same over the span tables (n at most the batch's grid capacity), with the
 // lines formed once in ``lines`` (8 bytes per entry each; z holds (z, ql) in
-// single precision under MIXED, ql in the plain path).  Declared weak, as the launches above are not:
-// host-only builds of the planner may leave it out.
+// single precision under MIXED, ql in the plain path).
 struct CagLines {
   double *w, *half, *wl, *z;
 };
-__attribute__((weak)) void launch_caglioti_spans(
-    bool mixed, const HChunk *eblocks, int64_t n_eblocks, const CrystalPlan *plan, const int32_t *crystal_order,
-    int64_t n_c, bool friedel, const int64_t *refl_offset, const double *ent_key, const int32_t *ent_idx,
-    const double *inten, double t0, double dt, int64_t n, double U, double V, double W, double eta, double window,
-    int64_t span_cap, CagLines lines, int32_t *span_first, int32_t *span_last, double *y, hipStream_t s);
+#if defined(__HIPCC__)
+void launch_caglioti_spans(bool mixed, const HChunk *eblocks, int64_t n_eblocks, const CrystalPlan *plan,
+                           const int32_t *crystal_order, int64_t n_c, bool friedel, const int64_t *refl_offset,
+                           const double *ent_key, const int32_t *ent_idx, const double *inten, double t0, double dt,
+                           int64_t n, double U, double V, double W, double eta, double window, int64_t span_cap,
+                           CagLines lines, int32_t *span_first, int32_t *span_last, double *y, hipStream_t s);
+#else  // host-only builds of the planner have no kernels
+template <class... Args>
+[[noreturn]] inline void launch_caglioti_spans(Args...) {
+  abort();
+}
+#endif
 // Atom gradients reduced over their partial rows and scattered to the
 // caller's order, and, in the same launch, dL/d(lattice) of every crystal
 // from its per-tile dL/dG* rows (written by launch_sf_bw).
