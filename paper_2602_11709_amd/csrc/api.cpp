@@ -15,6 +15,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <thread>
@@ -1013,16 +1014,16 @@ int xrd_batch_upload(xrd_batch *b, void *ws) {
   const WsLayout &L = b->ws;
   // The tables of a small batch are put together on the host and go in one
   // copy: a pageable copy of a few bytes costs 4-5 us of host time, and a batch
-  // has 13 (one crystal: 63 -> 15 us with the wait).  Larger ones go table by table, without
-  // the pass over host memory.
-  std::vector<char> staged;
-  if (L.tables <= kStageBytes) staged.resize((size_t)L.tables);
+  // has 13 (one crystal: 63 -> 15 us with the wait).  Larger ones, and all where
+  // the host has no memory to put them together, go table by table.
+  const std::unique_ptr<char[]> staged(L.tables <= kStageBytes ? new (std::nothrow) char[(size_t)L.tables]()
+                                                               : nullptr);
   hipError_t e = hipSuccess;
   auto up = [&](int64_t off, const auto &table) {
     const size_t bytes = sizeof(table[0]) * table.size();
     if (bytes == 0 || e != hipSuccess) return;
-    if (!staged.empty() && off < L.tables)
-      std::memcpy(staged.data() + off, table.data(), bytes);
+    if (staged && off < L.tables)
+      std::memcpy(staged.get() + off, table.data(), bytes);
     else
       e = hipMemcpyAsync(at<char>(ws, off), table.data(), bytes, hipMemcpyHostToDevice, s);
   };
@@ -1043,10 +1044,10 @@ int xrd_batch_upload(xrd_batch *b, void *ws) {
     up(L.sf_items_rec, b->sf_items_rec);
     up(L.rec_of, b->use_rec);
   }
-  if (!staged.empty() && e == hipSuccess)  // with a zero error flag
-    e = hipMemcpyAsync(ws, staged.data(), staged.size(), hipMemcpyHostToDevice, s);
+  if (staged && e == hipSuccess)  // with a zero error flag
+    e = hipMemcpyAsync(ws, staged.get(), (size_t)L.tables, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return fail(XRD_ERR_HIP, std::string("upload: ") + hipGetErrorString(e));
-  if (staged.empty()) launch_fill_i32(at<int32_t>(ws, L.err_flag), 1, 0, s);
+  if (!staged) launch_fill_i32(at<int32_t>(ws, L.err_flag), 1, 0, s);
   // pageable copies complete before return, but the tables stay owned by the
   // handle anyway; wait so that the handle may be destroyed right after
   e = hipStreamSynchronize(s);
